@@ -79,7 +79,7 @@ KERNEL_SOURCES = {
     "shadow_build": ["shadow.hip", "sampler.hpp", "philox.hpp"], "shadow_scan": ["shadow.hip"],
     "shadow_emit": ["shadow.hip"], "gather": ["gather.hip"],
     "aggregate": ["aggregate.hip", "relabel.hpp"],
-    "scatter": ["aggregate.hip", "train.hip"], "relu_mask": ["aggregate.hip"],
+    "scatter": ["aggregate.hip", "train.hip"],
     "gemm_fwd": ["gemm.hip", "train.hip"], "gemm_dw": ["gemm.hip", "train.hip"],
     "gemm_dx": ["gemm.hip", "train.hip"], "gemm_bwd": ["gemm.hip", "train.hip"],
     "softmax_xent": ["loss.hip"], "sgd": ["loss.hip"], "fill": ["common.hip"],
@@ -316,8 +316,7 @@ def launch_models(spec, keys, sz):
     head = not gin and L >= 2 and spec.dims[-1] <= 64
     top = L - 1 if head else L
     layered = {"aggregate": lambda k: k + 1, "gemm_fwd": lambda k: k + 1,
-               "gemm_dw": lambda k: 1, "gemm_bwd": lambda k: top - k, "scatter": lambda k: L - k,
-               "relu_mask": lambda k: L - k}
+               "gemm_dw": lambda k: 1, "gemm_bwd": lambda k: top - k, "scatter": lambda k: L - k}
     if gin:
         # two products per layer forward (agg W_a, M W_b); backward, layer L
         # down to 1: dW_b, dM, dW_a, then dAgg (not on layer 1)
@@ -415,8 +414,6 @@ def launch_models(spec, keys, sz):
                                f"({e:.0f} edge reads), {ns:.0f} gradient rows written"
                                + (" as bf16, masked by H1 (read)" if to16 else "") + ", "
                                + ("self path read, " if sage else "") + "lists and offsets")
-            elif name == "relu_mask":
-                m = ("hbm", ns * fi * 12, f"layer {l}: {ns:.0f} rows x {fi} x 4 B x 3")
         elif name in ("sample", "scans", "indices") and not spec.shadow:
             nd, ns, e = sz["hops"][k]
             f = spec.fanouts[k]
@@ -849,7 +846,7 @@ def measure(cfg, args, full):
         return None
 
     cal_ms = {k: sum(d[i] for _, d in cal) / cal_steps for i, k in enumerate(keys)}
-    modeled = {"gather", "aggregate", "gemm_fwd", "gemm_dw", "gemm_dx", "gemm_bwd", "scatter", "relu_mask",
+    modeled = {"gather", "aggregate", "gemm_fwd", "gemm_dw", "gemm_dx", "gemm_bwd", "scatter",
                "softmax_xent", "sgd", "shadow_build", "shadow_emit", "head"}
     if not spec.shadow:
         modeled |= {"sample", "scans", "indices"}

@@ -630,14 +630,14 @@ const char* gnn_version(void);
  * and events[2 i + 1], and names[i] receives the kernel's static name:
  * "begin", "sample", "scans", "indices" (neighbour sampling), "shadow_build",
  * "shadow_scan", "shadow_emit" (ShaDow), "gather", "aggregate", "gemm_fwd",
- * "gemm_dw", "gemm_dx", "scatter", "relu_mask", "softmax_xent", "sgd",
+ * "gemm_dw", "gemm_dx", "gemm_bwd", "scatter", "softmax_xent", "sgd",
  * "fill", "head", "work" (workload estimate), "cache_lookup", "cache_scan",
  * "cache_place", "cache_insert" (feature cache), "gat_scores", "gat_attend",
  * "gat_attend_bwd", "gat_score_grad", "gat_colsum", "gat_colsum_final" (GAT).
  * In a training step some launches carry neighbouring work: "begin"
  * also zeroes the gradient buffers, "gather" also compacts the last hop's
  * edges, "gemm_dx" also zeroes the rows the scatter adds into, and the GEMMs
- * read dZ through the ReLU mask (no "relu_mask" launch).  With `only` set, other kernels are not recorded.  A launch beyond
+ * read dZ through the ReLU mask.  With `only` set, other kernels are not recorded.  A launch beyond
  * `capacity`, or without a pair of events, is counted in `dropped` instead. */
 typedef struct {
   void* const* events;  /* [2 * capacity] hipEvent_t, created by the caller */

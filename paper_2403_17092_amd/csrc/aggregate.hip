@@ -307,11 +307,17 @@ aggregate_picks_kernel(SampleTail tail, const int32_t* __restrict__ src_nodes,
 // dH[u] += w_e dAgg[v] for every edge (v, u) (+ GCN / GIN self edge), fp32 atomics.
 // A group of LG lanes owns one edge; lane q handles features q, q + LG, ...,
 // so every atomic instruction covers LG consecutive floats of one row.
-template <int KIND, int LG>
+// MASK: features with mask[u] <= 0 are left alone (their sum is multiplied by
+// 0 anyway): no masking pass over dH follows, and the masked lanes issue no
+// atomics, which is what bounds this kernel.  The mask values of U edges are
+// loaded before the first of their atomics.
+template <int KIND, int LG, bool MASK>
 __global__ void __launch_bounds__(kThreads)
-scatter_kernel(BlockDev b, const float* __restrict__ dAgg, float* dH, int32_t F) {
+scatter_kernel(BlockDev b, const float* __restrict__ dAgg, float* dH, int32_t F,
+               const float* __restrict__ mask) {
   constexpr int G = 64 / LG;
   constexpr int NV = LG == 64 ? 4 : 1;  // F <= 256
+  constexpr int U = MASK ? 4 : 1;       // edges (of each group) per pass
   const int lane = lane_id();
   const int g = lane / LG, q = lane % LG;
   const int64_t v = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
@@ -336,7 +342,7 @@ scatter_kernel(BlockDev b, const float* __restrict__ dAgg, float* dH, int32_t F)
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
         const int f = q + j * LG;
-        if (f < F) unsafeAtomicAdd(o + f, w * d[j]);
+        if (f < F && (!MASK || mask[v * (int64_t)F + f] > 0.f)) unsafeAtomicAdd(o + f, w * d[j]);
       }
     }
   }
@@ -350,17 +356,28 @@ scatter_kernel(BlockDev b, const float* __restrict__ dAgg, float* dH, int32_t F)
       my_u = b.indices[e0 + base + lane];
       my_w = KIND == GNN_GCN ? rs * rsqrtf((float)b.occ[my_u]) : rs;
     }
-    for (int32_t l0 = 0; l0 < cc; l0 += G) {
-      const int32_t l = l0 + g;
-      const int32_t u = __shfl(my_u, l & 63, 64);
-      const float w = __shfl(my_w, l & 63, 64);
-      if (l < cc) {
-        float* o = dH + (int64_t)u * F;
+    for (int32_t l0 = 0; l0 < cc; l0 += G * U) {
+      int32_t u[U];
+      float w[U];
+      bool on[U][NV];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int32_t l = l0 + k * G + g;
+        u[k] = __shfl(my_u, l & 63, 64);
+        w[k] = __shfl(my_w, l & 63, 64);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
           const int f = q + j * LG;
-          if (f < F) unsafeAtomicAdd(o + f, w * d[j]);
+          on[k][j] = l < cc && f < F;
+          if (MASK && on[k][j]) on[k][j] = mask[(int64_t)u[k] * F + f] > 0.f;
         }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        float* o = dH + (int64_t)u[k] * F;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          if (on[k][j]) unsafeAtomicAdd(o + q + j * LG, w[k] * d[j]);
       }
     }
   }
@@ -481,25 +498,6 @@ scatter_t_kernel(BlockDev b, const int32_t* __restrict__ t_ptr, const int32_t* _
   }
 }
 
-__global__ void __launch_bounds__(kThreads)
-relu_mask_kernel(const int32_t* rows_dev, int32_t cap, const float4* __restrict__ h,
-                 float4* __restrict__ x, int32_t c4) {
-  int32_t rows = *rows_dev;
-  rows = rows > cap ? cap : rows;
-  const int64_t n = (int64_t)rows * c4;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * kThreads) {
-    const float4 m = h[i];
-    float4 y = x[i];
-    y.x = m.x > 0.f ? y.x : 0.f;
-    y.y = m.y > 0.f ? y.y : 0.f;
-    y.z = m.z > 0.f ? y.z : 0.f;
-    y.w = m.w > 0.f ? y.w : 0.f;
-    x[i] = y;
-  }
-}
-
-
 inline int pow2_at_least(int x) {
   int p = 1;
   while (p < x) p <<= 1;
@@ -582,19 +580,26 @@ int dispatch_aggregate_picks(const SampleTail& tail, int32_t cap_dst, const int3
 }
 
 template <int KIND>
-int dispatch_scatter(const gnn_block* blk, const float* dAgg, int32_t F, float* dH, hipStream_t st) {
+int dispatch_scatter(const gnn_block* blk, const float* dAgg, int32_t F, float* dH, const float* mask,
+                     hipStream_t st) {
   const int lg = F >= 64 ? 64 : pow2_at_least(F);
   const unsigned grid = (unsigned)std::max<int64_t>(1, ceil_div((int64_t)blk->cap_dst * 64, kThreads));
   BlockDev b = dev_view(blk);
-  auto go = [&](auto kernel) { launch("scatter", kernel, grid, kThreads, 0, st, b, dAgg, dH, F); };
+  auto go = [&](auto kernel) { launch("scatter", kernel, grid, kThreads, 0, st, b, dAgg, dH, F, mask); };
+#define GNN_SCATTER_CASE(N)                        \
+  case N:                                          \
+    if (mask) go(scatter_kernel<KIND, N, true>);   \
+    else go(scatter_kernel<KIND, N, false>);       \
+    break;
   switch (lg) {
-    case 4: go(scatter_kernel<KIND, 4>); break;
-    case 8: go(scatter_kernel<KIND, 8>); break;
-    case 16: go(scatter_kernel<KIND, 16>); break;
-    case 32: go(scatter_kernel<KIND, 32>); break;
-    case 64: go(scatter_kernel<KIND, 64>); break;
+    GNN_SCATTER_CASE(4)
+    GNN_SCATTER_CASE(8)
+    GNN_SCATTER_CASE(16)
+    GNN_SCATTER_CASE(32)
+    GNN_SCATTER_CASE(64)
     default: return fail(GNN_EINVAL, "scatter: feature width %d", F);
   }
+#undef GNN_SCATTER_CASE
   GNN_LAUNCH_CHECK("scatter");
   return GNN_OK;
 }
@@ -653,11 +658,11 @@ int launch_aggregate_picks(const SampleTail& tail, const gnn_block* blk, const v
 }
 
 int launch_scatter(const gnn_block* blk, int32_t kind, const float* dAgg, int32_t F, float* dH,
-                   hipStream_t st) {
+                   hipStream_t st, const float* mask) {
   if (blk->cap_dst == 0) return GNN_OK;
-  if (kind == GNN_GCN) return dispatch_scatter<GNN_GCN>(blk, dAgg, F, dH, st);
-  if (kind == GNN_GIN) return dispatch_scatter<GNN_GIN>(blk, dAgg, F, dH, st);
-  return dispatch_scatter<GNN_SAGE_MEAN>(blk, dAgg, F, dH, st);
+  if (kind == GNN_GCN) return dispatch_scatter<GNN_GCN>(blk, dAgg, F, dH, mask, st);
+  if (kind == GNN_GIN) return dispatch_scatter<GNN_GIN>(blk, dAgg, F, dH, mask, st);
+  return dispatch_scatter<GNN_SAGE_MEAN>(blk, dAgg, F, dH, mask, st);
 }
 
 int launch_scatter_t(const gnn_block* blk, int32_t kind, const int32_t* t_ptr, const int32_t* t_dst,
@@ -708,16 +713,5 @@ int launch_scatter_t(const gnn_block* blk, int32_t kind, const int32_t* t_ptr, c
   return fail(GNN_EINVAL, "scatter: feature width %d", F);
 #undef GNN_ST_CASE
 }
-
-int launch_relu_mask(const gnn_block* blk, const float* h, int32_t F, float* x, hipStream_t st) {
-  const int32_t c4 = F / 4;
-  int64_t blocks = ceil_div((int64_t)blk->cap_src * c4, kThreads * 4);
-  blocks = blocks < 1 ? 1 : (blocks > 4096 ? 4096 : blocks);
-  launch("relu_mask", relu_mask_kernel, (unsigned)blocks, kThreads, 0, st, blk->counts + 1,
-         blk->cap_src, reinterpret_cast<const float4*>(h), reinterpret_cast<float4*>(x), c4);
-  GNN_LAUNCH_CHECK("relu mask");
-  return GNN_OK;
-}
-
 
 }  // namespace gnn

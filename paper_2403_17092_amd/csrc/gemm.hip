@@ -71,7 +71,13 @@ struct Out {
   float* p1;
   int64_t ld0, ld1;
   int32_t split, axis;
+  const float* mask0;  // ReLU mask of part 0 (its stride), or null; plain stores only
 };
+
+__device__ __forceinline__ float4 relu_masked(float4 x, float4 m) {
+  return make_float4(m.x > 0.f ? x.x : 0.f, m.y > 0.f ? x.y : 0.f, m.z > 0.f ? x.z : 0.f,
+                     m.w > 0.f ? x.w : 0.f);
+}
 
 __device__ __forceinline__ void out_store(const Out& o, int64_t i, int64_t j, float x, int epilogue) {
   const bool second = o.axis == 0 ? (i >= o.split) : (j >= o.split);
@@ -79,9 +85,14 @@ __device__ __forceinline__ void out_store(const Out& o, int64_t i, int64_t j, fl
     if (o.axis == 0) i -= o.split;
     else j -= o.split;
   }
-  float* p = (second ? o.p1 : o.p0) + i * (second ? o.ld1 : o.ld0) + j;
-  if (epilogue == 2) unsafeAtomicAdd(p, x);
-  else *p = epilogue == 1 ? fmaxf(x, 0.f) : x;
+  const int64_t at = i * (second ? o.ld1 : o.ld0) + j;
+  float* p = (second ? o.p1 : o.p0) + at;
+  if (epilogue == 2) {
+    unsafeAtomicAdd(p, x);
+    return;
+  }
+  if (o.mask0 && !second && !(o.mask0[at] > 0.f)) x = 0.f;
+  *p = epilogue == 1 ? fmaxf(x, 0.f) : x;
 }
 
 // Four consecutive outputs (i, j .. j+3), j a multiple of 4; columns at or
@@ -96,8 +107,13 @@ __device__ __forceinline__ void out_store4(const Out& o, int64_t i, int64_t j, f
     if (o.axis == 0) ii -= o.split;
     else jj -= o.split;
   }
-  float* p = (second ? o.p1 : o.p0) + ii * (second ? o.ld1 : o.ld0) + jj;
+  const int64_t at = ii * (second ? o.ld1 : o.ld0) + jj;
+  float* p = (second ? o.p1 : o.p0) + at;
   if (one_part && j + 3 < n_lim && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+    if (o.mask0 && !second) {
+      const float* m = o.mask0 + at;
+      v = relu_masked(v, make_float4(m[0], m[1], m[2], m[3]));
+    }
     *reinterpret_cast<float4*>(p) = v;
     return;
   }
@@ -122,11 +138,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_from(const void* base, in
   bytes = bytes < 0 ? 0 : (bytes > 0x7FFFFFFF ? 0x7FFFFFFF : bytes);
   char* p = const_cast<char*>(static_cast<const char*>(base)) + o * ES;
   return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, (int)bytes, kBufWord3);
-}
-
-__device__ __forceinline__ float4 relu_masked(float4 x, float4 m) {
-  return make_float4(m.x > 0.f ? x.x : 0.f, m.y > 0.f ? x.y : 0.f, m.z > 0.f ? x.z : 0.f,
-                     m.w > 0.f ? x.w : 0.f);
 }
 
 // Four consecutive elements at byte offset `off` of resource r; element e
@@ -599,7 +610,7 @@ int plan_gemm(const MatView& A, const MatView& B, const OutView& C, int32_t m_ca
   }
   const int64_t blocks = gz > 1 ? ceil_div(gz, kXcds) * kXcds * gm * gn : gm8 * gn;
   if (blocks > INT32_MAX / 4) return fail(GNN_EINVAL, "gemm: grid too large");
-  Out o{C.p0, C.p1 ? C.p1 : C.p0, C.ld0, C.p1 ? C.ld1 : C.ld0, C.split, C.axis};
+  Out o{C.p0, C.p1 ? C.p1 : C.p0, C.ld0, C.p1 ? C.ld1 : C.ld0, C.split, C.axis, C.mask0};
   // physical extents: A is [m x k] (A^T: [k x m]), B is [k x n] (B^T: [n x k])
   const int64_t a_rows = A.trans ? k_cap : m_cap, a_cols = A.trans ? m_cap : k_cap;
   const int64_t b_rows = B.trans ? N : k_cap, b_cols = B.trans ? k_cap : N;

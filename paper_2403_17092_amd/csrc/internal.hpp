@@ -173,9 +173,10 @@ int launch_aggregate_picks(const SampleTail& tail, const gnn_block* blk, const v
                            int32_t dtype, int32_t F, int64_t n_rows, int64_t ld_h, void* out,
                            int32_t out_ld, hipStream_t st, int32_t out_dtype = GNN_F32,
                            const WtJob* wt = nullptr);
-// dH[idx_e] += w_e dAgg[v] (+ GCN self edge) with fp32 atomics.
+// dH[idx_e] += w_e dAgg[v] (+ GCN self edge) with fp32 atomics; with mask
+// ([n_src x F]) only into the features with mask > 0.
 int launch_scatter(const gnn_block* blk, int32_t kind, const float* dAgg, int32_t F, float* dH,
-                   hipStream_t st);
+                   hipStream_t st, const float* mask = nullptr);
 // The same backward as a gather over the block's transpose (t_ptr, t_dst):
 // every row u < n_src of dH is written once; SAGE rows u < n_dst must already
 // hold the self path (they are added to).  F a multiple of 4, at most 256.
@@ -184,8 +185,6 @@ int launch_scatter(const gnn_block* blk, int32_t kind, const float* dAgg, int32_
 int launch_scatter_t(const gnn_block* blk, int32_t kind, const int32_t* t_ptr, const int32_t* t_dst,
                      const float* dAgg, int32_t F, float* dH, hipStream_t st,
                      const float* mask = nullptr, uint16_t* out16 = nullptr);
-// x[i] *= (h[i] > 0) over rows < counts[1] (src count) of a [rows x F] matrix.
-int launch_relu_mask(const gnn_block* blk, const float* h, int32_t F, float* x, hipStream_t st);
 
 // GAT layer (gat.hip).  T rows have stride ldt (F rounded up to 4); s holds
 // (a_l . T_u, a_r . T_u) per src row u, stats (m_v, 1 / normaliser) per dst
@@ -239,6 +238,9 @@ struct OutView {
   const int32_t* zero_lo = nullptr;
   const int32_t* zero_hi = nullptr;
   int32_t zero_cap = 0;
+  // optional (plain stores): part 0's element (i, j) is written as 0 unless
+  // mask0[i * ld0 + j] > 0
+  const float* mask0 = nullptr;
   // optional: fill ranges done by the same launch (outside the GEMM's output)
   FillPair fills;
   // products on bf16 operands (both factors rounded to nearest even) with

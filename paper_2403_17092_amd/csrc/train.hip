@@ -156,8 +156,10 @@ int layer_fwd_impl(const gnn_block* blk, int32_t kind, const void* H_in, int32_t
 // dW must be zero on entry (the reduction over rows is atomic).
 // dZ_mask (optional): this layer's ReLU output H_out; dZ is then the
 // gradient w.r.t. H_out and is masked by H_out > 0 as the GEMMs read it.
-// mask_relu: mask the produced dH_in by H_in > 0 in a pass of its own (the
-// training step leaves that to the next layer's GEMMs instead).
+// mask_relu (without the transpose): the produced dH_in is masked by H_in > 0
+// as it is written, the self path by the product's store and the edges' shares
+// as they are added (the training step leaves the mask to the gather, or to
+// the next layer's GEMMs).
 // tr (optional): the block's transpose; the input gradient is then gathered
 // over it (every row written once) instead of scattered with atomics into
 // zeroed rows.
@@ -257,6 +259,8 @@ int layer_bwd_impl(const gnn_block* blk, int32_t kind, int32_t F_in, const float
   B2.ld = F_out;
   B2.trans = 1;
   const bool gather = tr && tr->t_ptr;
+  if (mask_relu && gather) return fail(GNN_EINVAL, "layer backward: the gather takes its own mask");
+  const float* in_mask = mask_relu ? H_in : nullptr;
   if (!gather) {
     C2.zero_p = dH_in;
     C2.zero_ld = F_in;
@@ -271,6 +275,7 @@ int layer_bwd_impl(const gnn_block* blk, int32_t kind, int32_t F_in, const float
     C2.ld1 = F_in;
     C2.axis = 1;
     C2.split = F_in;
+    C2.mask0 = in_mask;
     C2.zero_lo = blk->counts;
   } else {
     C2.p0 = dAgg;
@@ -293,12 +298,9 @@ int layer_bwd_impl(const gnn_block* blk, int32_t kind, int32_t F_in, const float
     return rc;
   }
   if (dH16 && !gather) return fail(GNN_EINVAL, "layer backward: bf16 input gradient needs the transpose");
-  if (int rc = gather ? launch_scatter_t(blk, kind, tr->t_ptr, tr->t_dst, dAgg, F_in, dH_in, st,
-                                         dH16 ? dH16_mask : dH_mask, dH16)
-                      : launch_scatter(blk, kind, dAgg, F_in, dH_in, st))
-    return rc;
-  if (mask_relu) return launch_relu_mask(blk, H_in, F_in, dH_in, st);
-  return GNN_OK;
+  return gather ? launch_scatter_t(blk, kind, tr->t_ptr, tr->t_dst, dAgg, F_in, dH_in, st,
+                                   dH16 ? dH16_mask : dH_mask, dH16)
+                : launch_scatter(blk, kind, dAgg, F_in, dH_in, st, in_mask);
 }
 
 int check_block(const gnn_block* b, const char* who) {
