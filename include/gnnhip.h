@@ -167,7 +167,7 @@ int gnn_block_caps(int32_t B, const int32_t* fanouts /*host*/, int32_t L, int64_
                    int32_t* cap_dst /*host[L]*/, int32_t* cap_src /*host[L]*/,
                    int64_t* cap_edges /*host[L]*/);
 
-/* Scratch bytes gnn_sample_blocks needs for these sizes (16 bytes per graph
+/* Scratch bytes gnn_sample_blocks needs for these sizes (12 bytes per graph
  * node of state kept between calls, see the conventions above, plus per-call
  * space). */
 size_t gnn_sample_workspace_bytes(int32_t B, const int32_t* fanouts /*host*/, int32_t L, int64_t N);

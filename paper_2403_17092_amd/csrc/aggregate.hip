@@ -284,7 +284,7 @@ aggregate_picks_kernel(SampleTail tail, const int32_t* __restrict__ src_nodes,
     // a fanout within the group: lane q loads pick q beside the count (the
     // edge list is then read in one pass, edge l by lane l)
     const bool pre = j.fanout <= LG;
-    const int32_t pk = pre && q < j.fanout ? picks[q] : -1;
+    const int32_t pk = pre && q < j.fanout ? pick_node(picks[q]) : -1;
     const int32_t c = j.kcount[v];
     const int32_t sv = src_nodes[v];
     float xs[C::VEC];
@@ -293,7 +293,7 @@ aggregate_picks_kernel(SampleTail tail, const int32_t* __restrict__ src_nodes,
     float acc[C::VEC];
     zero<C::VEC>(acc);
     auto edge = [&](int32_t l, int32_t* row, float* w) {
-      const int32_t key = pre ? pk : picks[l];
+      const int32_t key = pre ? pk : pick_node(picks[l]);
       const int32_t r = valid(key) ? key : row0;
       *row = valid(r) ? r : -1;
       *w = 1.f;

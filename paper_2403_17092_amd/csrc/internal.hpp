@@ -123,7 +123,7 @@ size_t sample_scratch_bytes(const int32_t* cap_dst, const int32_t* cap_src,
 // Transpose buffers of one block (src -> dst lists), see TransposeJob.
 struct BlockTranspose {
   int32_t* t_ptr = nullptr;  // [cap_src + 1]
-  int32_t* t_cur = nullptr;  // [cap_src]
+  int32_t* rank = nullptr;   // [cap_edges] an edge's place among its src node's edges
   int32_t* t_dst = nullptr;  // [cap_edges]
 };
 // tr (optional): per hop h < L - 1 with t_ptr set, the call also builds the
@@ -132,11 +132,13 @@ struct BlockTranspose {
 // was a sampling call whose last step prepared this one, and fewer than
 // kChainCalls calls have been chained since a call that was not; the begin
 // launch is then skipped (unless there are fills to do).
+// beside: the call runs beside another stream's work, and takes fewer, longer
+// workgroups.
 int sample_blocks_impl(const gnn_csr* csr, const int32_t* seeds, int32_t B,
                        const int32_t* fanouts, int32_t L, uint64_t rng_key, gnn_block* blocks,
                        void* ws, size_t ws_bytes, const FillRange* extra, int n_extra,
                        SampleTail* tail, hipStream_t st, const BlockTranspose* tr = nullptr,
-                       bool chained = false);
+                       bool chained = false, bool beside = false);
 
 // ---- ShaDow (shadow.hip) ------------------------------------------------------
 int shadow_caps(int32_t B, int32_t fanout, int32_t hops, int32_t* cap_nodes, int64_t* cap_edges);

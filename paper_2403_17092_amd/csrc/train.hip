@@ -494,7 +494,7 @@ int plan_step(const gnn_model* m, int32_t x_dtype, int32_t B, const int32_t* fan
       BlockTranspose t;
       if (h < L - 1) {
         t.t_ptr = c.take<int32_t>((size_t)b.cap_src + 1);
-        t.t_cur = c.take<int32_t>((size_t)std::max(1, b.cap_src));
+        t.rank = c.take<int32_t>((size_t)std::max<int64_t>(1, b.cap_edges));
         t.t_dst = c.take<int32_t>((size_t)std::max<int64_t>(1, b.cap_edges));
       }
       if (s == slot) {
@@ -1283,7 +1283,7 @@ int gnn_train_sample(const gnn_model* m, const gnn_csr* csr, const void* X, int3
   const bool fuse_tail = m->kind == GNN_SAGE_MEAN;
   if (int rc = sample_blocks_impl(csr, seeds, B, fanouts, m->num_layers, rng_key, p.blocks,
                                   p.sample_ws, p.sample_ws_bytes, nullptr, 0,
-                                  fuse_tail ? &tail : nullptr, st, p.tr))
+                                  fuse_tail ? &tail : nullptr, st, p.tr, false, true))
     return rc;
   // layer 1's aggregation needs the blocks and the features only, not the
   // weights: it is part of this call
