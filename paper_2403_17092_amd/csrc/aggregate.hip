@@ -395,6 +395,7 @@ scatter_kernel(BlockDev b, const float* __restrict__ dAgg, float* dH, int32_t F,
 // the next layer down's pre-activation gradient, so that its products read
 // it without a mask; 2 the same, written instead as bf16 (nearest even) to
 // out16 (same layout), ready for a product on bf16 operands.
+//
 template <int KIND, int LG, int CPL, int U, int OUT>
 __global__ void __launch_bounds__(kThreads)
 scatter_t_kernel(BlockDev b, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_dst,
@@ -495,6 +496,183 @@ scatter_t_kernel(BlockDev b, const int32_t* __restrict__ t_ptr, const int32_t* _
         *reinterpret_cast<float4*>(dH + u * (int64_t)F + 4 * ch) = make_float4(y[0], y[1], y[2], y[3]);
       }
     }
+  }
+}
+
+// The same gather for blocks with long lists.  A hub's list is a chain of
+// hundreds of dependent batches for one group (scatter_t_kernel over 95.8K rows
+// and 171K edges of a power-law block: 69 us, most of them waiting for a few
+// rows; this kernel: 37), so lists longer than kLongList are put off, and after
+// its other rows the workgroup takes them together, the groups' shares added up
+// through LDS in group order.  Its registers cost it a wave per SIMD, 1-2 us
+// where no list is long (41K edges, 163,840 at the capacity: the longest have
+// ~100), so it is taken from kLongEdges edges at the capacity on; ShaDow's union
+// block, whose rows end at a component's size, keeps the other.
+constexpr int32_t kLongList = 64;
+constexpr int64_t kLongEdges = 1 << 18;
+constexpr int32_t kLongRows = 128;  // rows a workgroup can put off (more are done at once)
+
+template <int KIND, int LG, int CPL, int U, int OUT>
+__global__ void __launch_bounds__(kThreads)
+scatter_long_kernel(BlockDev b, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_dst,
+                 const float* __restrict__ dAgg, float* __restrict__ dH, int32_t F,
+                 const float* __restrict__ mask, uint16_t* __restrict__ out16) {
+  constexpr int NG = kThreads / LG;  // groups of the workgroup
+  __shared__ float4 part[kThreads * CPL];
+  __shared__ int32_t long_rows[kLongRows];
+  __shared__ int32_t n_long;
+  const int q = lane_id() % LG;
+  const int gi = threadIdx.x / LG;
+  const int64_t n_src = b.counts[1];
+  const int32_t n_dst = b.counts[0];
+  const int32_t cpr = F / 4;
+  if (threadIdx.x == 0) n_long = 0;
+  __syncthreads();
+
+  // chunk k of this lane: q + k LG (live if below cpr)
+  auto load_row = [&](int64_t u, float4 (&self)[CPL], float4 (&m)[CPL]) {
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      const int ch = q + k * LG;
+      const bool ok = ch < cpr;
+      self[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      m[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (ok && u < n_dst) {
+        if (KIND == GNN_SAGE_MEAN) self[k] = reinterpret_cast<const float4*>(dH + u * (int64_t)F)[ch];
+        else self[k] = reinterpret_cast<const float4*>(dAgg + u * (int64_t)F)[ch];
+      }
+      if (OUT != 0 && ok) m[k] = reinterpret_cast<const float4*>(mask + u * (int64_t)F)[ch];
+    }
+  };
+  // edges [from, c) of the list at l0, LG at a time every `step`, one per lane, then U rows in flight
+  auto add_edges = [&](int32_t l0, int32_t from, int32_t c, int32_t step, float ru, float (&acc)[CPL][4]) {
+    for (int32_t base = from; base < c; base += step) {
+      const int32_t cc = c - base < LG ? c - base : LG;
+      int32_t my_v = 0;
+      float my_w = 0.f;
+      if (q < cc) {
+        my_v = t_dst[l0 + base + q];
+        const int32_t cv = b.indptr[my_v + 1] - b.indptr[my_v];
+        my_w = KIND == GNN_GCN ? ru * rsqrtf((float)(cv + 1)) : (KIND == GNN_GIN ? 1.f : 1.f / (float)cv);
+      }
+      for (int32_t k0 = 0; k0 < cc; k0 += U) {
+        float4 x[U][CPL];
+        float wv[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+          const int32_t l = k0 + e;
+          const int32_t v = __shfl(my_v, l & (LG - 1), LG);
+          const float w = __shfl(my_w, l & (LG - 1), LG);
+          wv[e] = l < cc ? w : 0.f;
+#pragma unroll
+          for (int k = 0; k < CPL; ++k) {
+            const int ch = q + k * LG;
+            x[e][k] = l < cc && ch < cpr ? reinterpret_cast<const float4*>(dAgg + (int64_t)v * F)[ch]
+                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+#pragma unroll
+          for (int k = 0; k < CPL; ++k) {
+            acc[k][0] += wv[e] * x[e][k].x;
+            acc[k][1] += wv[e] * x[e][k].y;
+            acc[k][2] += wv[e] * x[e][k].z;
+            acc[k][3] += wv[e] * x[e][k].w;
+          }
+      }
+    }
+  };
+  auto write_row = [&](int64_t u, float ru, const float4 (&self)[CPL], const float4 (&m)[CPL],
+                       const float (&acc)[CPL][4]) {
+    float ws = 1.f;  // weight of the self row (SAGE: the self path as written)
+    if (KIND == GNN_GCN && u < n_dst)
+      ws = ru * rsqrtf((float)(b.indptr[u + 1] - b.indptr[u] + 1));
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      const int ch = q + k * LG;
+      if (ch >= cpr) continue;
+      float y[4] = {acc[k][0], acc[k][1], acc[k][2], acc[k][3]};
+      if (u < n_dst) {
+        y[0] += ws * self[k].x;
+        y[1] += ws * self[k].y;
+        y[2] += ws * self[k].z;
+        y[3] += ws * self[k].w;
+      }
+      if constexpr (OUT != 0) {
+        y[0] = m[k].x > 0.f ? y[0] : 0.f;
+        y[1] = m[k].y > 0.f ? y[1] : 0.f;
+        y[2] = m[k].z > 0.f ? y[2] : 0.f;
+        y[3] = m[k].w > 0.f ? y[3] : 0.f;
+      }
+      if constexpr (OUT == 2) {
+        uint32_t w2[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const __bf16 lo = (__bf16)y[2 * i], hi = (__bf16)y[2 * i + 1];
+          w2[i] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
+        }
+        *reinterpret_cast<uint2*>(out16 + u * (int64_t)F + 4 * ch) = make_uint2(w2[0], w2[1]);
+      } else {
+        *reinterpret_cast<float4*>(dH + u * (int64_t)F + 4 * ch) = make_float4(y[0], y[1], y[2], y[3]);
+      }
+    }
+  };
+
+  const int64_t stride = (int64_t)gridDim.x * NG;
+  for (int64_t u = (int64_t)blockIdx.x * NG + gi; u < n_src; u += stride) {
+    float4 self[CPL], m[CPL];
+    load_row(u, self, m);
+    const int32_t l0 = t_ptr[u], c = t_ptr[u + 1] - l0;
+    if (c > kLongList) {
+      int32_t at = 0;
+      if (q == 0) at = atomicAdd(&n_long, 1);
+      at = __shfl(at, 0, LG);
+      if (at < kLongRows) {
+        if (q == 0) long_rows[at] = (int32_t)u;
+        continue;
+      }
+    }
+    float ru = 1.f;
+    if (KIND == GNN_GCN) ru = rsqrtf((float)b.occ[u]);
+    float acc[CPL][4];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
+    add_edges(l0, 0, c, LG, ru, acc);
+    write_row(u, ru, self, m, acc);
+  }
+  __syncthreads();
+  const int32_t rows = n_long < kLongRows ? n_long : kLongRows;
+  for (int32_t r = 0; r < rows; ++r) {
+    const int64_t u = long_rows[r];
+    const int32_t l0 = t_ptr[u], c = t_ptr[u + 1] - l0;
+    float ru = 1.f;
+    if (KIND == GNN_GCN) ru = rsqrtf((float)b.occ[u]);
+    float acc[CPL][4];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
+    add_edges(l0, gi * LG, c, NG * LG, ru, acc);
+#pragma unroll
+    for (int k = 0; k < CPL; ++k)
+      part[(gi * CPL + k) * LG + q] = make_float4(acc[k][0], acc[k][1], acc[k][2], acc[k][3]);
+    __syncthreads();
+    if (gi == 0) {
+      float4 self[CPL], m[CPL];
+      load_row(u, self, m);
+      // (groups past the list's last batch of LG edges added nothing)
+      const int32_t used = (c + LG - 1) / LG < NG ? (c + LG - 1) / LG : NG;
+      for (int32_t g = 1; g < used; ++g)
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) {
+          const float4 x = part[(g * CPL + k) * LG + q];
+          acc[k][0] += x.x;
+          acc[k][1] += x.y;
+          acc[k][2] += x.z;
+          acc[k][3] += x.w;
+        }
+      write_row(u, ru, self, m, acc);
+    }
+    __syncthreads();
   }
 }
 
@@ -686,22 +864,28 @@ int launch_scatter_t(const gnn_block* blk, int32_t kind, const int32_t* t_ptr, c
     launch("scatter", kernel, grid, kThreads, 0, st, b, t_ptr, t_dst, dAgg, dH, F, mask, out16);
   };
   constexpr int SAGE = GNN_SAGE_MEAN;
-#define GNN_ST_CASE(N, C, U)                                                               \
-  if (lg == N && cpl == C) {                                                               \
-    if (mask) {                                                                            \
-      if (kind == GNN_GCN) {                                                               \
-        if (out16) go(scatter_t_kernel<GNN_GCN, N, C, U, 2>);                              \
-        else go(scatter_t_kernel<GNN_GCN, N, C, U, 1>);                                    \
-      } else if (out16) {                                                                  \
-        go(scatter_t_kernel<SAGE, N, C, U, 2>);                                            \
-      } else {                                                                             \
-        go(scatter_t_kernel<SAGE, N, C, U, 1>);                                            \
-      }                                                                                    \
-    } else if (kind == GNN_GCN) go(scatter_t_kernel<GNN_GCN, N, C, U, 0>);                 \
-    else if (kind == GNN_GIN) go(scatter_t_kernel<GNN_GIN, N, C, U, 0>);                   \
-    else go(scatter_t_kernel<SAGE, N, C, U, 0>);                                           \
-    GNN_LAUNCH_CHECK("scatter");                                                           \
-    return GNN_OK;                                                                         \
+  const bool lng = t_ptr != blk->indptr && blk->cap_edges >= kLongEdges;
+#define GNN_ST_GO(K, N, C, U, O)                    \
+  do {                                              \
+    if (lng) go(scatter_long_kernel<K, N, C, U, O>);  \
+    else go(scatter_t_kernel<K, N, C, U, O>);         \
+  } while (0)
+#define GNN_ST_CASE(N, C, U)                                  \
+  if (lg == N && cpl == C) {                                  \
+    if (mask) {                                               \
+      if (kind == GNN_GCN) {                                  \
+        if (out16) GNN_ST_GO(GNN_GCN, N, C, U, 2);            \
+        else GNN_ST_GO(GNN_GCN, N, C, U, 1);                  \
+      } else if (out16) {                                     \
+        GNN_ST_GO(SAGE, N, C, U, 2);                          \
+      } else {                                                \
+        GNN_ST_GO(SAGE, N, C, U, 1);                          \
+      }                                                       \
+    } else if (kind == GNN_GCN) GNN_ST_GO(GNN_GCN, N, C, U, 0); \
+    else if (kind == GNN_GIN) GNN_ST_GO(GNN_GIN, N, C, U, 0); \
+    else GNN_ST_GO(SAGE, N, C, U, 0);                         \
+    GNN_LAUNCH_CHECK("scatter");                              \
+    return GNN_OK;                                            \
   }
   GNN_ST_CASE(1, 1, 4)
   GNN_ST_CASE(2, 1, 4)
@@ -712,6 +896,7 @@ int launch_scatter_t(const gnn_block* blk, int32_t kind, const int32_t* t_ptr, c
   GNN_ST_CASE(16, 4, 2)
   return fail(GNN_EINVAL, "scatter: feature width %d", F);
 #undef GNN_ST_CASE
+#undef GNN_ST_GO
 }
 
 }  // namespace gnn
