@@ -193,6 +193,23 @@ struct GemmArgs {
   FillPair fills;
 };
 
+// What the blocks past gemm_blocks do: the ZeroJob's rows and the fills.
+__device__ __forceinline__ void side_jobs(const GemmArgs& ga, int32_t bid, int32_t nbid) {
+  const ZeroJob zj = ga.zj;
+  if (zj.p) {
+    const int32_t lo = zj.lo ? *zj.lo : 0;
+    int32_t hi = *zj.hi;
+    hi = hi > zj.cap ? zj.cap : hi;
+    const int64_t n = lo < hi ? (int64_t)(hi - lo) * zj.c4 : 0;
+    const int64_t stride = (int64_t)(nbid - ga.gemm_blocks) * kThreads;
+    for (int64_t i = (int64_t)(bid - ga.gemm_blocks) * kThreads + threadIdx.x; i < n; i += stride) {
+      const int64_t r = lo + i / zj.c4, c = i % zj.c4;
+      zj.p[r * zj.ld4 + c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  run_fills(ga.fills, bid - ga.gemm_blocks, nbid - ga.gemm_blocks, kThreads);
+}
+
 // LDS floats of an instance with TN-column tiles: two stages of both
 // operands, or the output tile
 template <int FL, int TN>
@@ -216,24 +233,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga, int32_t bid, int32
   const int32_t* k_dev = ga.k_dev;
   const int32_t epilogue = ga.epilogue, min_chunk = ga.min_chunk, nsplit = ga.nsplit;
   const int32_t gemm_blocks = ga.gemm_blocks;
-  const ZeroJob zj = ga.zj;
   constexpr bool AT = FL & kAT, BT = FL & kBT, AV = FL & kAV, BV = FL & kBV;
   constexpr bool AM = FL & kAM, BM_ = FL & kBM, BF = FL & kBF, AH = FL & kAH, BH = FL & kBH;
   constexpr int AES = AH ? 2 : 4, BES = BH ? 2 : 4;  // element bytes
   static_assert(!(AM && AH) && !(BM_ && BH), "masks go with fp32 operands");
   if (bid >= gemm_blocks) {
-    if (zj.p) {
-      const int32_t lo = zj.lo ? *zj.lo : 0;
-      int32_t hi = *zj.hi;
-      hi = hi > zj.cap ? zj.cap : hi;
-      const int64_t n = lo < hi ? (int64_t)(hi - lo) * zj.c4 : 0;
-      const int64_t stride = (int64_t)(nbid - gemm_blocks) * kThreads;
-      for (int64_t i = (int64_t)(bid - gemm_blocks) * kThreads + threadIdx.x; i < n; i += stride) {
-        const int64_t r = lo + i / zj.c4, c = i % zj.c4;
-        zj.p[r * zj.ld4 + c] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-    run_fills(ga.fills, bid - gemm_blocks, nbid - gemm_blocks, kThreads);
+    side_jobs(ga, bid, nbid);
     return;
   }
   constexpr bool AROW = !AT, BROW = BT;   // [row][k] layouts
@@ -557,6 +562,8 @@ __global__ void __launch_bounds__(kThreads) gemm_pair_kernel(GemmArgs g1, GemmAr
   else gemm_body<FL2, TN2>(g2, b - part1, (int32_t)gridDim.x - part1, smem);
 }
 
+#include "gemm_split.hpp"
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
@@ -664,8 +671,70 @@ int launch_empty(const GemmPlan& pl, hipStream_t st) {
   return launch_fill(fr, n, st);
 }
 
+// Products over at least this many rows at the capacity (the reduction's, for a
+// weight gradient) run on the bf16 matrix units (gemm_split.hpp).  The line lies
+// where the live rows of such a capacity, a third of it or more, fill the GPU
+// with its larger tiles: at 41K-109K live rows they took 0.63-0.9 of the fp32
+// tiles' time, at 19.8K (65,536 at the capacity) 1.06 times, at 4.9K-7K 1.0-1.6.
+constexpr int64_t kSplitRows = 3 << 15;
+
+// Whether the plan's product takes the split form.
+bool split_ok(const GemmPlan& pl) {
+  const GemmArgs& a = pl.args;
+  const int shape = pl.code & ~(kAV | kBV);
+  if (pl.empty || a.A.ld > (1 << 21) || a.B.ld > (1 << 21)) return false;
+  // narrow products pad most of a 64-column tile, short ones most of a slab
+  if (shape == 0 || shape == kBT || shape == (kBT | kAM))
+    return a.epilogue != 2 && a.m_cap >= kSplitRows && a.N >= 48 && a.k_cap >= 64;
+  // (a weight gradient of fewer than four 128 x 128 tiles has too many chunks
+  // adding into each: 200 x 128 over 95,782 rows 64 us in fp32 tiles, 76 here)
+  if (shape == kAT || shape == (kAT | kBM))
+    return a.epilogue == 2 && a.nsplit > 1 && a.k_cap >= kSplitRows &&
+           ceil_div(a.m_cap, 128) * ceil_div(a.N, 128) >= 4;
+  return false;
+}
+
+// The plan's grid and flags for the split form (tn: tile columns, occ:
+// workgroups per CU).
+void plan_split(GemmPlan* pl, int tn, int occ) {
+  GemmArgs& a = pl->args;
+  const int64_t side = pl->blocks - a.gemm_blocks;
+  const int64_t fit = (int64_t)device_cu_count() * occ / kXcds * kXcds;
+  int64_t blocks = std::max<int64_t>(kXcds, fit);
+  if (pl->code & kAT) {
+    a.nsplit = 256;
+    a.min_chunk = 256;
+    pl->code &= ~(kAV | kBV);  // (k is the outer axis of both)
+  } else {
+    blocks = std::min(blocks, ceil_div(ceil_div(a.m_cap, 128), kXcds) * kXcds * ceil_div(a.N, tn));
+    const int vec = pl->code & kBT ? ((pl->code & kAV) && (pl->code & kBV) ? kAV | kBV : 0) : pl->code & kAV;
+    pl->code = (pl->code & ~(kAV | kBV)) | vec;
+  }
+  a.gemm_blocks = (int32_t)blocks;
+  pl->blocks = blocks + side;
+}
+
+int launch_split(GemmPlan pl, const char* name, hipStream_t st) {
+  plan_split(&pl, 64, pl.code & (kAM | kBM | kAT) ? 2 : 3);
+  auto go = [&](auto kernel) { launch(name, kernel, dim3((unsigned)pl.blocks), kThreads, 0, st, pl.args); };
+  switch (pl.code) {
+    case 0: go(split_kernel<0>); break;
+    case kAV: go(split_kernel<kAV>); break;
+    case kBT: go(split_kernel<kBT>); break;
+    case kBT | kAV | kBV: go(split_kernel<kBT | kAV | kBV>); break;
+    case kBT | kAM: go(split_kernel<kBT | kAM>); break;
+    case kBT | kAM | kAV | kBV: go(split_kernel<kBT | kAM | kAV | kBV>); break;
+    case kAT: go(split_dw_kernel<kAT>); break;
+    case kAT | kBM: go(split_dw_kernel<kAT | kBM>); break;
+    default: return fail(GNN_EINVAL, "gemm: unsupported operand combination of the split form");
+  }
+  GNN_LAUNCH_CHECK("gemm");
+  return GNN_OK;
+}
+
 int launch_plan(const GemmPlan& pl, const char* name, hipStream_t st) {
   if (pl.empty) return launch_empty(pl, st);
+  if (split_ok(pl)) return launch_split(pl, name, st);
   auto go = [&](auto kernel) { launch(name, kernel, dim3((unsigned)pl.blocks), kThreads, 0, st, pl.args); };
   // instances: forward (A X, B weights), dW (A^T, B = dZ, maybe masked),
   // dX (A = dZ maybe masked, B^T weights); vector and scalar loads each;
@@ -746,6 +815,18 @@ int launch_gemm_pair(const GemmSpec& p1, const GemmSpec& p2, const char* name, h
   if (!pair) {
     if (int rc = launch_plan(a, p1.name, st)) return rc;
     return launch_plan(b, p2.name, st);
+  }
+  if (split_ok(a) && split_ok(b)) {
+    plan_split(&a, 128, 2);
+    plan_split(&b, 128, 2);
+    const int64_t first = ceil_div(a.blocks, kXcds) * kXcds;
+    auto go = [&](auto kernel) {
+      launch(name, kernel, dim3((unsigned)(first + b.blocks)), kThreads, 0, st, a.args, b.args, (int32_t)first);
+    };
+    if (a.code == kAT) go(split_pair_kernel<kAT, kDx>);
+    else go(split_pair_kernel<kAT | kBM, kDxM>);
+    GNN_LAUNCH_CHECK("gemm pair");
+    return GNN_OK;
   }
   if (a.tn != 64) return fail(GNN_EINVAL, "gemm pair: the weight gradient takes 64-wide tiles");
   const int64_t part1 = ceil_div(a.blocks, kXcds) * kXcds;  // whole XCD rounds
