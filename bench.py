@@ -80,12 +80,14 @@ KERNEL_SOURCES = {
     "shadow_emit": ["shadow.hip"], "gather": ["gather.hip"],
     "aggregate": ["aggregate.hip", "relabel.hpp"],
     "scatter": ["aggregate.hip", "train.hip"],
-    "gemm_fwd": ["gemm.hip", "train.hip"], "gemm_dw": ["gemm.hip", "train.hip"],
-    "gemm_dx": ["gemm.hip", "train.hip"], "gemm_bwd": ["gemm.hip", "train.hip"],
+    "gemm_fwd": ["gemm.hip", "gemm_split.hpp", "train.hip"],
+    "gemm_dw": ["gemm.hip", "gemm_split.hpp", "train.hip"],
+    "gemm_dx": ["gemm.hip", "gemm_split.hpp", "train.hip"],
+    "gemm_bwd": ["gemm.hip", "gemm_split.hpp", "train.hip"],
     "softmax_xent": ["loss.hip"], "sgd": ["loss.hip"], "fill": ["common.hip"],
     "head": ["head.hip"],
     "gat_scores": ["gat.hip"], "gat_attend": ["gat.hip"], "gat_attend_bwd": ["gat.hip"],
-    "gat_score_grad": ["gat.hip"], "gat_colsum": ["gat.hip"], "gat_colsum_final": ["gat.hip"],
+    "gat_colsum": ["gat.hip"], "gat_colsum_final": ["gat.hip"],
     "work": ["dlb.hip"],
 }
 
@@ -215,30 +217,28 @@ def gat_launch_model(spec, name, k, layer_block, sz):
         return ("hbm", u * fo * 12 + r * 16 + nd * fo * 8,
                 f"layer {l}: {u:.0f} distinct rows of T read and of dT added to, scores, ids and two "
                 f"score-gradient adds of {r:.0f} edges; {nd:.0f} output-gradient rows (and mask)")
-    if name == "gat_score_grad":
-        l = L - k
-        nd, ns, e, fi, fo = dims(l)
-        return ("hbm", ns * (fo * 8 + 8), f"layer {l}: {ns:.0f} rows of dT updated from 2 scores")
     if name == "gemm_dw":
-        if k >= L - 1:  # layer 1: dW = G^T dOut, then dW += hh [a_l; a_r]
+        if k == L - 1:  # layer 1: dW = G^T dOut
             nd, ns, e, fi, fo = dims(1)
-            f, what = [(2.0 * nd * fi * fo, "G^T dOut"), (2.0 * fi * 2 * fo, "hh a")][k - (L - 1)]
-            return ("mfma", f, f"layer 1: {what}, {f:.3g} flops")
+            return ("mfma", 2.0 * nd * fi * fo, f"layer 1: G^T dOut, 2 x {nd:.0f} x {fi} x {fo} flops")
         l = L - k
         nd, ns, e, fi, fo = dims(l)
         return ("mfma", 2.0 * ns * fi * fo, f"layer {l}: dW = H^T dT, 2 x {ns:.0f} x {fi} x {fo} flops")
     if name == "gat_colsum":
-        # [ds_l | ds_r]^T T per layer (da); layer 1 also H^T [ds_l | ds_r]
-        if k == L:
-            nd, ns, e, fi, fo = dims(1)
-            return ("hbm", ns * (fi * 4 + 8) + 256 * 2048,
-                    f"layer 1: {ns:.0f} input rows of {fi} x 4 B and 2 scores read, 256 parts written")
+        # [ds_l | ds_r]^T T per layer (da); layer 1 also H^T [ds_l | ds_r], the
+        # others the score gradients' share of dT
         l = L - k
         nd, ns, e, fi, fo = dims(l)
-        return ("hbm", ns * (fo * 4 + 8) + 256 * 2048,
-                f"layer {l}: {ns:.0f} rows of T ({fo} x 4 B) and 2 scores read, 256 parts written")
+        if l == 1:
+            return ("hbm", ns * ((fo + fi) * 4 + 8) + 2 * 256 * 2048,
+                    f"layer 1: {ns:.0f} rows of T ({fo} x 4 B), input rows of {fi} x 4 B and 2 scores "
+                    f"read, 2 x 256 parts written")
+        return ("hbm", ns * (fo * 12 + 8) + 256 * 2048,
+                f"layer {l}: {ns:.0f} rows of T ({fo} x 4 B) and 2 scores read, rows of dT updated, "
+                f"256 parts written")
     if name == "gat_colsum_final":
-        return ("hbm", 256 * 2048, "256 parts of 2 x 256 column sums read")
+        jobs = 2 if k == L - 1 else 1
+        return ("hbm", jobs * 256 * 2048, f"{jobs} x 256 parts of 2 x 256 column sums read")
     if name == "gemm_dx":
         l = L - k
         nd, ns, e, fi, fo = dims(l)
@@ -851,7 +851,7 @@ def measure(cfg, args, full):
     if not spec.shadow:
         modeled |= {"sample", "scans", "indices"}
     if spec.kind == "gat":
-        modeled |= {"gat_scores", "gat_attend", "gat_attend_bwd", "gat_score_grad", "gat_colsum",
+        modeled |= {"gat_scores", "gat_attend", "gat_attend_bwd", "gat_colsum",
                     "gat_colsum_final"}
     dom = max((k for k in keys if k.split("#")[0] in modeled), key=lambda k: cal_ms[k])
     dom_name, dom_occ = dom.split("#")[0], int(dom.split("#")[1])

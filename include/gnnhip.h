@@ -633,7 +633,7 @@ const char* gnn_version(void);
  * "gemm_dw", "gemm_dx", "gemm_bwd", "scatter", "softmax_xent", "sgd",
  * "fill", "head", "work" (workload estimate), "cache_lookup", "cache_scan",
  * "cache_place", "cache_insert" (feature cache), "gat_scores", "gat_attend",
- * "gat_attend_bwd", "gat_score_grad", "gat_colsum", "gat_colsum_final" (GAT).
+ * "gat_attend_bwd", "gat_colsum", "gat_colsum_final" (GAT).
  * In a training step some launches carry neighbouring work: "begin"
  * also zeroes the gradient buffers, "gather" also compacts the last hop's
  * edges, "gemm_dx" also zeroes the rows the scatter adds into, and the GEMMs

@@ -275,40 +275,78 @@ attend_bwd_kernel(EdgeView b, const float* __restrict__ T, int32_t ldt, const fl
   }
 }
 
-// dT_u += ds_r[u] a_r + [u < n_dst] ds_l[u] a_l for every src row u.
-__global__ void __launch_bounds__(kThreads)
-score_grad_kernel(const int32_t* counts, const float* __restrict__ a, int32_t F,
-                  const float* __restrict__ ds, float* __restrict__ dT, int32_t ldt) {
+// dT_u += ds_r[u] a_r + [u < n_dst] ds_l[u] a_l for every src row u (block of blocks).
+struct ScoreGradJob {
+  const float* a = nullptr;  // null: nothing to do
+  const float* ds = nullptr;
+  float* dT = nullptr;
+  int32_t ldt = 0, F = 0;
+};
+__device__ __forceinline__ void score_grad(const ScoreGradJob& j, const int32_t* counts, uint32_t block,
+                                           uint32_t blocks) {
   const int64_t n_src = counts[1], n_dst = counts[0];
-  const int64_t total = n_src * F;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * kThreads) {
-    const int64_t u = i / F;
-    const int32_t f = (int32_t)(i - u * F);
-    float x = ds[2 * u + 1] * a[F + f];
-    if (u < n_dst) x += ds[2 * u] * a[f];
-    dT[u * ldt + f] += x;
+  const int64_t total = n_src * j.F;
+  for (int64_t i = (int64_t)block * kThreads + threadIdx.x; i < total; i += (int64_t)blocks * kThreads) {
+    const int64_t u = i / j.F;
+    const int32_t f = (int32_t)(i - u * j.F);
+    float x = j.ds[2 * u + 1] * j.a[j.F + f];
+    if (u < n_dst) x += j.ds[2 * u] * j.a[f];
+    j.dT[u * j.ldt + f] += x;
   }
 }
 
-// [ds_l | ds_r]^T X in two passes: colsum_part_kernel<QL> gives each of its
-// workgroups a chunk of rows (256 / QL row groups of QL lanes, a lane per
-// 4-column chunk) and writes the chunk's two column sums to part[block]
+// [ds_l | ds_r]^T X in two passes: colsum_kernel gives each of a job's
+// kColsumParts workgroups a chunk of rows (256 / QL row groups of QL lanes, a
+// lane per 4-column chunk) and writes the chunk's two column sums to its part
 // (2 x 256 floats; zeros for an empty chunk); colsum_final_kernel adds the
-// parts in block order.  No atomics, and the result does not depend on timing.
+// parts in block order.  The sums themselves do not depend on timing.  Two jobs
+// (the score vectors' gradient and layer 1's input sums) and the score gradients
+// share the launches: each pass alone is half latency (layer 1 of a 45K-row
+// block: 12.0 + 4.0 and 7.6 + 4.1 us in turn and 4.3 for the product that added the
+// sums' outer products, 12.8 + 5.3 together).
 constexpr int kColsumParts = 256;
+constexpr int kColsumJobs = 2;
 
-template <int QL>
-__global__ void __launch_bounds__(kThreads)
-colsum_part_kernel(const int32_t* n_dev, int32_t cap, const float* __restrict__ w,
-                   const float* __restrict__ X, int64_t ld, int32_t F, float* __restrict__ part) {
-  constexpr int RG = kThreads / QL;
-  __shared__ float4 red[2][RG][QL];
-  int32_t n = *n_dev;
-  n = n > cap ? cap : n;
-  const int q = threadIdx.x % QL, rg = threadIdx.x / QL;
-  const int64_t chunk = ((int64_t)n + gridDim.x - 1) / gridDim.x;
-  const int64_t r0 = (int64_t)blockIdx.x * chunk;
+struct ColsumJob {
+  const float* X = nullptr;
+  int64_t ld = 0;
+  int32_t F = 0;
+  int32_t ql = 1;  // lanes per row, a power of two
+  float* out = nullptr;  // out[c * oc + f * of]
+  int64_t oc = 0, of = 0;
+  // optional: W[f, j] += sum_l[f] a[j] + sum_r[f] a[Fo + j], j < Fo (atomics: a
+  // product adds into the same rows)
+  const float* a = nullptr;
+  float* W = nullptr;
+  int32_t Fo = 0;
+};
+struct ColsumArgs {
+  ColsumJob job[kColsumJobs];
+  int32_t jobs = 0;
+  const int32_t* counts = nullptr;  // rows: counts[1], at most cap
+  int32_t cap = 0;
+  const float* w = nullptr;  // (ds_l, ds_r) per row
+  float* part = nullptr;
+  ScoreGradJob sg;
+};
+
+__global__ void __launch_bounds__(kThreads) colsum_kernel(ColsumArgs a) {
+  __shared__ float4 red[2][kThreads];
+  const int jb = blockIdx.x / kColsumParts;
+  if (jb >= a.jobs) {
+    score_grad(a.sg, a.counts, blockIdx.x - a.jobs * kColsumParts, gridDim.x - a.jobs * kColsumParts);
+    return;
+  }
+  const ColsumJob j = a.job[jb];
+  const int block = blockIdx.x % kColsumParts;
+  const int QL = j.ql, RG = kThreads / QL;
+  const int32_t F = j.F;
+  const float* X = j.X;
+  int32_t n = a.counts[1];
+  n = n > a.cap ? a.cap : n;
+  const int q = threadIdx.x & (QL - 1), rg = threadIdx.x / QL;
+  const int64_t chunk = ((int64_t)n + kColsumParts - 1) / kColsumParts;
+  const int64_t r0 = (int64_t)block * chunk;
   const int64_t r1 = r0 + chunk < n ? r0 + chunk : n;
   float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = a0;
   auto add = [&](float4 x, float w0, float w1) {
@@ -329,45 +367,61 @@ colsum_part_kernel(const int32_t* n_dev, int32_t cap, const float* __restrict__ 
       float2 wv[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        x[i] = load_cols(X, ld, u + i * RG, q, F);
-        wv[i] = reinterpret_cast<const float2*>(w)[u + i * RG];
+        x[i] = load_cols(X, j.ld, u + i * RG, q, F);
+        wv[i] = reinterpret_cast<const float2*>(a.w)[u + i * RG];
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) add(x[i], wv[i].x, wv[i].y);
     }
     for (; u < r1; u += RG) {
-      const float2 wv = reinterpret_cast<const float2*>(w)[u];
-      add(load_cols(X, ld, u, q, F), wv.x, wv.y);
+      const float2 wv = reinterpret_cast<const float2*>(a.w)[u];
+      add(load_cols(X, j.ld, u, q, F), wv.x, wv.y);
     }
   }
-  red[0][rg][q] = a0;
-  red[1][rg][q] = a1;
+  red[0][threadIdx.x] = a0;
+  red[1][threadIdx.x] = a1;
   __syncthreads();
-  // thread t: column sum t of c = t / 256... one float per thread: 2 x 4 QL values
+  // one float per thread: 2 x 4 QL values
+  float* part = a.part + ((int64_t)jb * kColsumParts + block) * 512;
   for (int t = threadIdx.x; t < 2 * 4 * QL; t += kThreads) {
     const int c = t / (4 * QL), f = t % (4 * QL);
     float acc = 0.f;
     for (int g = 0; g < RG; ++g) {
-      const float4 v = red[c][g][f / 4];
+      const float4 v = red[c][g * QL + f / 4];
       acc += (f & 3) == 0 ? v.x : ((f & 3) == 1 ? v.y : ((f & 3) == 2 ? v.z : v.w));
     }
-    part[(int64_t)blockIdx.x * 512 + c * 256 + f] = acc;
+    part[c * 256 + f] = acc;
   }
 }
 
-// out[c * oc + f * of] = sum over the parts of part[b][c][f]: a wave per
-// output, lane l over parts l, l + 64, ..., then a fixed-order wave sum.
-__global__ void __launch_bounds__(kThreads)
-colsum_final_kernel(const float* __restrict__ part, int32_t nparts, int32_t F, float* out, int64_t oc,
-                    int64_t of) {
+// A wave per column of a job: lane l adds parts l, l + 64, ..., then a
+// fixed-order wave sum.
+__global__ void __launch_bounds__(kThreads) colsum_final_kernel(ColsumArgs a) {
   const int lane = lane_id();
-  const int64_t t = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
-  if (t >= 2 * F) return;
-  const int c = (int)(t / F), f = (int)(t % F);
-  float acc = 0.f;
-  for (int b = lane; b < nparts; b += 64) acc += part[(int64_t)b * 512 + c * 256 + f];
-  acc = wave_sum(acc);
-  if (lane == 0) out[c * oc + f * of] = acc;
+  int32_t f = (int32_t)(((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6);
+  int jb = 0;
+  if (f >= a.job[0].F) {
+    f -= a.job[0].F;
+    jb = 1;
+  }
+  if (jb >= a.jobs || f >= a.job[jb].F) return;
+  const ColsumJob j = a.job[jb];
+  const float* part = a.part + (int64_t)jb * kColsumParts * 512 + f;
+  float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+  for (int b = 0; b < kColsumParts / 64; ++b) {
+    s0 += part[(int64_t)(lane + 64 * b) * 512];
+    s1 += part[(int64_t)(lane + 64 * b) * 512 + 256];
+  }
+  s0 = wave_sum(s0);
+  s1 = wave_sum(s1);
+  if (lane == 0 && j.out) {
+    j.out[f * j.of] = s0;
+    j.out[j.oc + f * j.of] = s1;
+  }
+  if (j.W)
+    for (int32_t c = lane; c < j.Fo; c += 64)
+      unsafeAtomicAdd(j.W + (int64_t)f * j.Fo + c, s0 * j.a[c] + s1 * j.a[j.Fo + c]);
 }
 
 inline int lanes_for(int32_t F) {
@@ -476,38 +530,33 @@ int launch_gat_attend_bwd(const gnn_block* blk, const float* T, int32_t ldt, con
   return GNN_OK;
 }
 
-size_t gat_colsum_part_floats() { return (size_t)kColsumParts * 512; }
+size_t gat_colsum_part_floats() { return (size_t)kColsumJobs * kColsumParts * 512; }
 
-int launch_gat_colsum2(const int32_t* n_dev, int32_t cap, const float* w, const float* X, int64_t ld,
-                       int32_t F, float* part, float* out, int64_t oc, int64_t of, hipStream_t st) {
-  if (int rc = check_f(F, "GAT column sums")) return rc;
-  const int ql = lanes_for(F);
-  auto go = [&](auto kernel) {
-    launch("gat_colsum", kernel, kColsumParts, kThreads, 0, st, n_dev, std::max(0, cap), w, X, ld, F,
-           part);
-  };
-  switch (ql) {
-    case 1: go(colsum_part_kernel<1>); break;
-    case 2: go(colsum_part_kernel<2>); break;
-    case 4: go(colsum_part_kernel<4>); break;
-    case 8: go(colsum_part_kernel<8>); break;
-    case 16: go(colsum_part_kernel<16>); break;
-    case 32: go(colsum_part_kernel<32>); break;
-    default: go(colsum_part_kernel<64>); break;
+int launch_gat_colsum(const gnn_block* blk, const float* ds, const GatColsum* jobs, int n, float* part,
+                      const float* sg_a, float* dT, int32_t ldt, int32_t F, hipStream_t st) {
+  if (n < 1 || n > kColsumJobs) return fail(GNN_EINVAL, "GAT column sums: %d jobs", n);
+  ColsumArgs a;
+  a.jobs = n;
+  a.counts = blk->counts;
+  a.cap = std::max(0, blk->cap_src);
+  a.w = ds;
+  a.part = part;
+  int64_t waves = 0;
+  for (int k = 0; k < n; ++k) {
+    const GatColsum& g = jobs[k];
+    if (int rc = check_f(g.F, "GAT column sums")) return rc;
+    a.job[k] = ColsumJob{g.X, g.ld, g.F, lanes_for(g.F), g.out, g.F, 1, g.a, g.W, g.Fo};
+    waves += g.F;
   }
+  unsigned grid = (unsigned)(n * kColsumParts);
+  if (sg_a && blk->cap_src > 0) {
+    a.sg = ScoreGradJob{sg_a, ds, dT, ldt, F};
+    grid += std::min(1024u, stride_grid((int64_t)blk->cap_src * F));
+  }
+  launch("gat_colsum", colsum_kernel, grid, kThreads, 0, st, a);
   GNN_LAUNCH_CHECK("GAT column sums");
-  launch("gat_colsum_final", colsum_final_kernel, wave_grid(2 * (int64_t)F), kThreads, 0, st,
-         (const float*)part, (int32_t)kColsumParts, F, out, oc, of);
+  launch("gat_colsum_final", colsum_final_kernel, wave_grid(waves), kThreads, 0, st, a);
   GNN_LAUNCH_CHECK("GAT column sums");
-  return GNN_OK;
-}
-
-int launch_gat_score_grad(const gnn_block* blk, const float* a, int32_t F, const float* ds, float* dT,
-                          int32_t ldt, hipStream_t st) {
-  if (blk->cap_src == 0) return GNN_OK;
-  launch("gat_score_grad", score_grad_kernel, stride_grid((int64_t)blk->cap_src * F), kThreads, 0,
-         st, (const int32_t*)blk->counts, a, F, ds, dT, ldt);
-  GNN_LAUNCH_CHECK("GAT score gradient");
   return GNN_OK;
 }
 

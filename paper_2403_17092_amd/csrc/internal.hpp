@@ -200,14 +200,25 @@ int launch_gat_attend(const gnn_block* blk, const float* T, int32_t ldt, const f
 int launch_gat_attend_bwd(const gnn_block* blk, const float* T, int32_t ldt, const float* s,
                           const float* stats, const float* dout, int64_t ld_do, const float* mask,
                           int32_t F, float* dT, float* ds, hipStream_t st);
-int launch_gat_score_grad(const gnn_block* blk, const float* a, int32_t F, const float* ds, float* dT,
-                          int32_t ldt, hipStream_t st);
-// out[c * oc + f * of] = sum over rows u < min(*n_dev, cap) of w[2u + c] X[u, f]
-// (c = 0, 1; f < F; X row stride ld), the [ds_l | ds_r]^T X products, in a
-// fixed order through `part` (gat_colsum_part_floats() floats).
+// Column sums [ds_l | ds_r]^T X over the block's src rows: out[c * F + f] = sum
+// over u of ds[2u + c] X[u, f] (c = 0, 1; f < F; X row stride ld; out may be
+// null), in a fixed order through `part` (gat_colsum_part_floats() floats).
+// With W: W[f, j] += sum_0[f] a[j] + sum_1[f] a[Fo + j], j < Fo, by atomics.
+struct GatColsum {
+  const float* X;
+  int64_t ld;
+  int32_t F;
+  float* out;
+  const float* a;
+  float* W;
+  int32_t Fo;
+};
 size_t gat_colsum_part_floats();
-int launch_gat_colsum2(const int32_t* n_dev, int32_t cap, const float* w, const float* X, int64_t ld,
-                       int32_t F, float* part, float* out, int64_t oc, int64_t of, hipStream_t st);
+// One or two of them; with sg_a the same launch also adds the score gradients'
+// share to dT (row stride ldt): dT_u += ds_r[u] a_r + [u < n_dst] ds_l[u] a_l,
+// sg_a = [a_l; a_r] of width F.
+int launch_gat_colsum(const gnn_block* blk, const float* ds, const GatColsum* jobs, int n, float* part,
+                      const float* sg_a, float* dT, int32_t ldt, int32_t F, hipStream_t st);
 
 // ---- GEMM (gemm.hip) --------------------------------------------------------
 // A row-major fp32 matrix; `trans` reads it transposed (logical (i, j) is

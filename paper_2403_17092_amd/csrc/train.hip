@@ -379,7 +379,6 @@ struct StepPlan {
   float* stats[GNN_MAX_LAYERS];
   float* dz;
   float* ds;
-  float* hh;    // GAT layer 1: [H^T ds_l | H^T ds_r] (F_in x 2)
   float* part;  // GAT: per-workgroup column sums (gat_colsum_part_floats())
   float* row_loss;
   // output layer and loss in one launch (head.hip); its weight gradient comes
@@ -453,7 +452,6 @@ void carve_model(Carver& c, const gnn_model* m, int32_t x_dtype, int32_t B, Step
   p->w1t = w1t ? c.take<uint16_t>((size_t)thin_fwd_wt_elems(k1)) : nullptr;
   p->dz = dz_elems ? c.take<float>(dz_elems) : nullptr;
   p->ds = ds_elems ? c.take<float>(ds_elems) : nullptr;
-  p->hh = gat ? c.take<float>(2 * (size_t)m->dims[0]) : nullptr;
   p->part = gat ? c.take<float>(gat_colsum_part_floats()) : nullptr;
   p->row_loss = c.take<float>((size_t)std::max(1, B));
   // (the partials are part of the workspace whenever the widths allow the
@@ -609,8 +607,9 @@ int update_weights(const gnn_model* m, const StepPlan& p, float lr, int32_t B, f
 // ds_l[u] a_l gives dW = G^T dOut + (H^T ds_l) a_l^T + (H^T ds_r) a_r^T, with
 // G_v = sum_u alpha_vu H_u the attention-weighted input rows (an aggregation
 // over the block, no atomics).  The score gradients come from the same
-// backward pass over the edges with its dT output switched off.
-// zeroed: ds and hh were zeroed by an earlier launch of the step.
+// backward pass over the edges with its dT output switched off; the two rank-1
+// terms are added as the sums H^T ds_l and H^T ds_r are finished.
+// zeroed: ds was zeroed by an earlier launch of the step.
 int gat_layer1_bwd(const gnn_model* m, const StepPlan& p, const gnn_block* blk, const float* dout,
                    int64_t ld_do, const float* mask, hipStream_t st, bool zeroed) {
   const int32_t Fi = m->dims[0], Fo = m->dims[1], ldt = pad4(Fo);
@@ -620,20 +619,18 @@ int gat_layer1_bwd(const gnn_model* m, const StepPlan& p, const gnn_block* blk, 
   const float* hin = p.x[0];
   float* G = p.dz;
   if (!zeroed) {
-    const FillRange zr[2] = {{p.ds, (int64_t)std::max(1, blk->cap_src) * 2, 0}, {p.hh, (int64_t)Fi * 2, 0}};
-    if (int rc = launch_fill(zr, 2, st)) return rc;
+    const FillRange zr[1] = {{p.ds, (int64_t)std::max(1, blk->cap_src) * 2, 0}};
+    if (int rc = launch_fill(zr, 1, st)) return rc;
   }
   if (int rc = launch_gat_attend_bwd(blk, p.z[0], ldt, p.s[0], p.stats[0], dout, ld_do, mask, Fo,
                                      nullptr, p.ds, st))
     return rc;
   // G: the forward's attention (same scores, so the same weights) over H
   if (int rc = launch_gat_attend(blk, hin, Fi, p.s[0], Fi, 0, G, p.stats[0], st)) return rc;
-  // [da_l; da_r] = [ds_l | ds_r]^T T and hh = H^T [ds_l | ds_r]
-  if (int rc = launch_gat_colsum2(blk->counts + 1, blk->cap_src, p.ds, p.z[0], ldt, Fo, p.part,
-                                  dw + (int64_t)Fi * Fo, Fo, 1, st))
-    return rc;
-  if (int rc = launch_gat_colsum2(blk->counts + 1, blk->cap_src, p.ds, hin, Fi, Fi, p.part, p.hh, 1, 2, st))
-    return rc;
+  // [da_l; da_r] = [ds_l | ds_r]^T T, and dW += (H^T ds_l) a_l^T + (H^T ds_r) a_r^T
+  const GatColsum jobs[2] = {{p.z[0], ldt, Fo, dw + (int64_t)Fi * Fo, nullptr, nullptr, 0},
+                             {hin, Fi, Fi, nullptr, a, dw, Fo}};
+  if (int rc = launch_gat_colsum(blk, p.ds, jobs, 2, p.part, nullptr, nullptr, 0, 0, st)) return rc;
   // dW = G^T dOut (dOut masked by the layer's ReLU output), reduced over the dst rows
   MatView A, Bm;
   OutView C;
@@ -645,18 +642,7 @@ int gat_layer1_bwd(const gnn_model* m, const StepPlan& p, const gnn_block* blk, 
   Bm.mask = mask;
   C.p0 = dw;
   C.ld0 = Fo;
-  if (int rc = launch_gemm(A, Bm, C, Fi, Fo, blk->cap_dst, nullptr, blk->counts, 2, 256, "gemm_dw", st))
-    return rc;
-  // dW += hh [a_l; a_r]
-  MatView A2, B2;
-  OutView C2;
-  A2.p = p.hh;
-  A2.ld = 2;
-  B2.p = a;
-  B2.ld = Fo;
-  C2.p0 = dw;
-  C2.ld0 = Fo;
-  return launch_gemm(A2, B2, C2, Fi, Fo, 2, nullptr, nullptr, 2, 0, "gemm_dw", st);
+  return launch_gemm(A, Bm, C, Fi, Fo, blk->cap_dst, nullptr, blk->counts, 2, 256, "gemm_dw", st);
 }
 
 // GAT forward and backward (gat.hip for the attention; GEMMs for T = H W and
@@ -747,10 +733,10 @@ int run_gat(const gnn_model* m, const StepPlan& p, const void* X, int32_t x_dtyp
     if (int rc = launch_gat_attend_bwd(blk, p.z[l - 1], ldt, p.s[l - 1], p.stats[l - 1], dout, ld_do,
                                        mask, Fo, p.dz, p.ds, st))
       return rc;
-    if (int rc = launch_gat_score_grad(blk, W + (int64_t)Fi * Fo, Fo, p.ds, p.dz, ldt, st)) return rc;
-    // [da_l; da_r] = [ds_l | ds_r]^T T (ds_l is 0 past the dst rows)
-    if (int rc = launch_gat_colsum2(blk->counts + 1, blk->cap_src, p.ds, p.z[l - 1], ldt, Fo, p.part,
-                                    dw + (int64_t)Fi * Fo, Fo, 1, st))
+    // dT's share of the score gradients, and [da_l; da_r] = [ds_l | ds_r]^T T
+    // (ds_l is 0 past the dst rows)
+    const GatColsum job{p.z[l - 1], ldt, Fo, dw + (int64_t)Fi * Fo, nullptr, nullptr, 0};
+    if (int rc = launch_gat_colsum(blk, p.ds, &job, 1, p.part, W + (int64_t)Fi * Fo, p.dz, ldt, Fo, st))
       return rc;
     // dW = H_in^T dT
     MatView A, Bm;
@@ -776,11 +762,9 @@ int run_gat(const gnn_model* m, const StepPlan& p, const void* X, int32_t x_dtyp
     C2.p0 = p.dh[l & 1];
     C2.ld0 = Fi;
     if (l == 2) {
-      // layer 1's ds and hh (ds is read no more by this layer; dT is, and is not zeroed)
-      const gnn_block* b1 = p.layer_blk[0];
-      const FillRange zr[2] = {{p.ds, (int64_t)std::max(1, b1->cap_src) * 2, 0},
-                               {p.hh, (int64_t)dims[0] * 2, 0}};
-      C2.fills = fill_pair(zr, 2);
+      // layer 1's ds (read no more by this layer; dT is, and is not zeroed)
+      const FillRange zr[1] = {{p.ds, (int64_t)std::max(1, p.layer_blk[0]->cap_src) * 2, 0}};
+      C2.fills = fill_pair(zr, 1);
     }
     if (int rc = launch_gemm(A2, B2, C2, blk->cap_src, Fi, Fo, blk->counts + 1, nullptr, 0, 0, "gemm_dx", st))
       return rc;
