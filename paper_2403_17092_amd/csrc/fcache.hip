@@ -98,12 +98,18 @@ __device__ __forceinline__ uint32_t fmix32(uint32_t h) {
 
 // Groups of G lanes, one requested row each (G >= the row's 16-byte chunks
 // where possible, so a row is one load per lane).
-// A set's first miss of the call goes to the workgroup's list in LDS; after
-// each pass over its rows the workgroup appends the list to the call's
-// touched list with one global atomic (one per set, from every workgroup,
-// serialised on the one counter: about 60K of them per call on the 111M-node
-// workload, 0.7 ms).  A pass adds at most one entry per lane group.
+// A set's first miss of the call goes to the workgroup's list in LDS, which is
+// appended to the call's touched list with one global atomic when it fills up
+// and at the end.  Device atomics on one address run one after the other (~17 ns
+// each): one per set took 0.7 ms for 60K of them, and one per workgroup and pass
+// (3.6K for 28K rows) beside two more for the statistics were what this launch
+// waited for beside the host link (its step 268 us, now 256 with kLookupBlocks
+// workgroups and the statistics taken from the scan).  A pass adds at most one entry per lane group.
 constexpr int kTouchedLds = kThreads;
+// Rows in flight (4 K to 16 K) to cover the host link's latency: 28K rows over a
+// 57 GB/s link, 10K of them misses of 400 bytes (71 us of transfer), took 264 us
+// a step with 256 workgroups, 259 with 512, 256 with 1024, 255 with 2048
+constexpr int64_t kLookupBlocks = 1024;
 
 template <int G>
 __global__ void __launch_bounds__(kThreads)
@@ -111,15 +117,13 @@ lookup_kernel(CacheView cv, const uint4* __restrict__ X, int64_t n_rows, int64_t
               const int32_t* __restrict__ ids, const int32_t* n_ids, int32_t cap,
               uint4* __restrict__ out, int64_t ld_out16, int32_t* __restrict__ miss_set,
               int32_t* __restrict__ touched, unsigned long long* stats, int* err) {
-  __shared__ int32_t red[2];
+  __shared__ int32_t invalid;
   __shared__ int32_t tl_n, tl_base;
   __shared__ int32_t tl[kTouchedLds];
-  if (threadIdx.x < 2) red[threadIdx.x] = 0;
-  if (threadIdx.x == 0) tl_n = 0;
+  if (threadIdx.x == 0) tl_n = invalid = 0;
   __syncthreads();
   // appends the workgroup's listed sets to the call's touched list (all threads)
   auto flush = [&]() {
-    __syncthreads();
     const int32_t m = tl_n < kTouchedLds ? tl_n : kTouchedLds;
     if (threadIdx.x == 0 && m > 0) tl_base = atomicAdd(&cv.hdr->touched, m);
     __syncthreads();
@@ -137,7 +141,6 @@ lookup_kernel(CacheView cv, const uint4* __restrict__ X, int64_t n_rows, int64_t
   const int lane = lane_id(), r = lane & (G - 1);
   const int64_t group = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / G;
   const int64_t groups = (int64_t)gridDim.x * (kThreads / G);
-  int32_t hits = 0, misses = 0;
   // every thread runs the same number of passes (the flushes synchronise the
   // workgroup); a group past the last request idles through its pass
   const int64_t passes = (n + groups - 1) / groups;
@@ -160,7 +163,6 @@ lookup_kernel(CacheView cv, const uint4* __restrict__ X, int64_t n_rows, int64_t
         if (r == 0) {
           cv.stamps[(int64_t)s * cv.W + way] = t;
           miss_set[i] = -1;
-          ++hits;
         }
       } else {
         if (valid) {
@@ -170,22 +172,26 @@ lookup_kernel(CacheView cv, const uint4* __restrict__ X, int64_t n_rows, int64_t
           for (int j = r; j < cv.cpr; j += G) dst[j] = make_uint4(0, 0, 0, 0);
         }
         if (r == 0) {
-          if (!valid) set_device_error(err, GNN_DEVERR_SEED_RANGE);
-          else if (atomicAdd(&cv.miss_cnt[s], 1) == 0)  // the set's first miss of the call
+          if (!valid) {
+            set_device_error(err, GNN_DEVERR_SEED_RANGE);
+            atomicAdd(&invalid, 1);
+          } else if (atomicAdd(&cv.miss_cnt[s], 1) == 0)  // the set's first miss of the call
             tl[atomicAdd(&tl_n, 1)] = s;
           miss_set[i] = valid ? s : -1;
-          ++misses;
         }
       }
     }
-    flush();
+    __syncthreads();
+    // room for the next pass's entries (every thread reads the count before
+    // any adds to it again)
+    const int32_t listed = tl_n;
+    __syncthreads();
+    if (pass + 1 == passes || listed > kTouchedLds - kThreads / G) flush();
   }
-  if (hits) atomicAdd(&red[0], hits);
-  if (misses) atomicAdd(&red[1], misses);
-  __syncthreads();
-  if (threadIdx.x == 0 && (red[0] | red[1])) {
-    atomicAdd(&stats[0], (unsigned long long)red[0]);
-    atomicAdd(&stats[1], (unsigned long long)red[1]);
+  // invalid ids count as misses; the scan counts the others
+  if (threadIdx.x == 0 && invalid) {
+    atomicAdd(&stats[0], 0ull - (unsigned long long)invalid);
+    atomicAdd(&stats[1], (unsigned long long)invalid);
   }
 }
 
@@ -195,12 +201,18 @@ lookup_kernel(CacheView cv, const uint4* __restrict__ X, int64_t n_rows, int64_t
 // workgroup walking ~60K sets took ~0.25 ms per call on the 111M-node
 // workload).  The touched count goes to the scratch.
 __global__ void __launch_bounds__(kThreads)
-scan_kernel(CacheView cv, CallScratch cs, int32_t cap) {
+scan_kernel(CacheView cv, CallScratch cs, const int32_t* n_ids, int32_t cap, unsigned long long* stats) {
   __shared__ int32_t wsum[kThreads / 64];
   __shared__ int32_t s_base;
   int32_t nt = cv.hdr->touched;
   nt = nt > cap ? cap : nt;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *cs.n_touched = nt;
+  // stats += (hits, misses): every request a hit, less the sets' misses (and,
+  // in the lookup, less the invalid ids)
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *cs.n_touched = nt;
+    const int32_t n = *n_ids;
+    atomicAdd(&stats[0], (unsigned long long)(n > cap ? cap : (n < 0 ? 0 : n)));
+  }
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   for (int64_t base = (int64_t)blockIdx.x * kThreads; base < nt; base += (int64_t)gridDim.x * kThreads) {
     const int64_t j = base + threadIdx.x;
@@ -215,7 +227,11 @@ scan_kernel(CacheView cv, CallScratch cs, int32_t cap) {
       before += w < wid ? wsum[w] : 0;
       total += wsum[w];
     }
-    if (threadIdx.x == 0) s_base = atomicAdd(&cv.hdr->list_next, total);
+    if (threadIdx.x == 0) {
+      s_base = atomicAdd(&cv.hdr->list_next, total);
+      atomicAdd(&stats[0], 0ull - (unsigned long long)total);
+      atomicAdd(&stats[1], (unsigned long long)total);
+    }
     __syncthreads();
     if (set >= 0) {
       cs.off[set] = s_base + before + inc - c;
@@ -394,7 +410,7 @@ int gnn_gather_cached(const gnn_feature_cache* c, const void* X, int64_t n_rows,
   const int64_t ld_x16 = ld_x * es / 16, ld_out16 = ld_out * es / 16;
   auto outp = static_cast<uint4*>(out);
   const int G = cpr > 32 ? 64 : (cpr > 16 ? 32 : 16);
-  const int64_t lblocks = std::min<int64_t>(8192, std::max<int64_t>(1, ceil_div((int64_t)cap * G, kThreads)));
+  const int64_t lblocks = std::min<int64_t>(kLookupBlocks, std::max<int64_t>(1, ceil_div((int64_t)cap * G, kThreads)));
   auto look = [&](auto kernel) {
     launch("cache_lookup", kernel, (unsigned)lblocks, kThreads, 0, st, v,
            static_cast<const uint4*>(X), n_rows, ld_x16, ids, n_ids, cap, outp, ld_out16,
@@ -405,7 +421,8 @@ int gnn_gather_cached(const gnn_feature_cache* c, const void* X, int64_t n_rows,
   else look(lookup_kernel<64>);
   GNN_LAUNCH_CHECK(who);
   const int64_t sblocks = std::min<int64_t>(512, std::max<int64_t>(1, ceil_div(cap, kThreads)));
-  launch("cache_scan", scan_kernel, (unsigned)sblocks, kThreads, 0, st, v, cs, cap);
+  launch("cache_scan", scan_kernel, (unsigned)sblocks, kThreads, 0, st, v, cs, n_ids, cap,
+         reinterpret_cast<unsigned long long*>(stats));
   GNN_LAUNCH_CHECK(who);
   const int64_t pblocks = std::min<int64_t>(2048, std::max<int64_t>(1, ceil_div(cap, kThreads)));
   launch("cache_place", place_kernel, (unsigned)pblocks, kThreads, 0, st, v, n_ids, cap, cs);
