@@ -43,10 +43,12 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kSampleThreads = 512;      // the last compaction's blocks
 constexpr int kSampleMaxBlocks = 2048;
-// beside another stream's work: one workgroup per CU leaves that work its share
-// (six pipelined steps of a 16M-node workload 1,389 -> 1,350 us; alone, its
-// serial step 255 -> 262 us)
-constexpr int kSampleBesideBlocks = 256;
+// beside another stream's work the wide form leaves that work its share of the
+// CUs (six pipelined steps of a 16M-node workload: 1,389 us uncapped, 1,356 with
+// 256 workgroups, 1,351 with 192, 1,378 with 128; alone, its serial step 255 ->
+// 262 us).  Narrow frontiers, a wave per node, are bound by their chain of loads
+// and keep their workgroups (three pipelined steps of 536 seeds 267 -> 238 us)
+constexpr int kSampleBesideBlocks = 192;
 constexpr int kIndexBlocksMax = 1024;
 // slots of a hop from which the sampling looks before its atomics
 constexpr int64_t kLookSlots = 1 << 16;
@@ -626,7 +628,7 @@ static int sample_hops(const gnn_csr* csr, const RP* rowptr, const int32_t* seed
     while (4 * P < f || (P < 16 && (int64_t)bk.cap_dst * P < 64 * 4096)) P *= 2;
     if ((int64_t)bk.cap_dst <= kResidentWaves) P = WAVE;
     const int64_t per_block = kThreads / P;
-    const int64_t sblocks = std::min<int64_t>(beside ? kSampleBesideBlocks : kSampleMaxBlocks,
+    const int64_t sblocks = std::min<int64_t>(beside && P < WAVE ? kSampleBesideBlocks : kSampleMaxBlocks,
                                               std::max<int64_t>(1, ceil_div(bk.cap_dst, per_block)));
     // extra blocks: hop h - 1's compaction and hop h - 2's transpose fill
     const TransposeJob tfill = tjob(h - 2);
